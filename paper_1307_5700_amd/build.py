@@ -28,6 +28,7 @@ SOURCES = {
     "rfi.hip": [],
     "dedisp.hip": [],
     "dedisp_u8.hip": [],
+    "dedisp_u8_mx.hip": [],
     "detect.hip": [],
     "median.hip": [],
     "mulaw.hip": [],

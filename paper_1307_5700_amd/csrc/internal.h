@@ -202,6 +202,41 @@ hipError_t dedisp_u8_prepare();
 // kernel's geometry; a.x 8-byte aligned with a.ld a multiple of 8.
 hipError_t launch_dedisp_u8(const DedispArgs& a, const int32_t* relb, size_t lds, hipStream_t s);
 
+// Matrix-core kernel for 8-bit data without cleaning (dedisp_u8_mx.hip): a
+// workgroup covers kMxBD DMs in groups of 16 and forms, per group, kMxW
+// columns of partial sums, of which up to kMxMaxBT are outputs; cells of
+// kMxCW channels, kMxCells of them per quarter of a step.
+constexpr int kMxJ = 9, kMxPieces = 4, kMxGroups = 2, kMxBD = 16 * kMxGroups;
+constexpr int kMxW = 16 * kMxJ * kMxPieces, kMxMaxBT = 512, kMxMinBT = 128;
+constexpr int kMxCW = 16, kMxCells = 684, kMxMaxSteps = 8, kMxMaxShifts = 16;
+constexpr int kMxLds = 2 * 4 * kMxCells * kMxCW + 4 * (kMxBD * (kMxW + 4) + 512);
+static_assert(kMxLds <= 160 * 1024, "LDS of a CU");
+// Tables of a plan, steps numbered over all partial sums.
+struct MxTables {
+  const int32_t* sbase;      // [blocks][cpad]: input sample of staged cell 0, less the tile's start
+  const int32_t* poff;       // [blocks][nsub][kMxBD]: first partial-sum column of a DM
+  const int2* hdr;           // [blocks][steps][groups][4]: a quarter's first cell, the step's shifts
+  const uint8_t* hot;        // [2][blocks][steps][groups][64][kMxCW]: bit q of a byte set for a channel
+                             // whose shift is q (second half: 8 + q)
+  const int32_t* moff;       // [blocks * kMxBD]: a DM's output is the column less moff
+  int32_t cpad, nsub, ns;    // padded channels; partial sums; steps of a partial sum
+  int32_t BT;                // outputs of a tile
+};
+struct MxSetup {
+  const int32_t* delays;
+  int32_t C, ndms, ns, nsub, cpad;
+  int32_t *sbase, *poff;
+  int2* hdr;
+  uint8_t* hot;
+  int32_t* moff;
+  int32_t* stats;            // [4]: largest poff; cells needed beyond BT; shifts; largest moff
+};
+hipError_t dedisp_u8_mx_prepare();
+hipError_t launch_mx_setup(const MxSetup& p, int nblk, hipStream_t s);
+// One single-shot launch (no ring, phase 0): a.n_dblocks and a.n_ttiles in
+// this kernel's geometry.
+hipError_t launch_dedisp_u8_mx(const DedispArgs& a, const MxTables& t, hipStream_t s);
+
 // Writes the chunk's last min(L, R) cleaned samples into the ring at the
 // positions given by the beam's device-side sample count, then advances the
 // beam's device-side position (seen_dev: [seen, first output of the chunk,

@@ -103,6 +103,12 @@ struct mb_plan {
   int rs8 = 0;
   size_t lds8 = 0;
   int32_t* d_relb8 = nullptr;
+  // and its matrix-core form, when the delays fit that kernel's tile: one
+  // device allocation with the tables
+  bool u8_mx = false;
+  char* mx_mem = nullptr;
+  MxTables mx{};
+  int32_t mx_moff = 0;         // largest output offset of a DM within its block
 };
 
 struct mb_beam {
@@ -207,6 +213,71 @@ void u8_geometry(mb_plan& p) {
   p.u8_int = p.desc.in_dtype == MB_U8 && rs <= kU8RS && lds <= kMaxLds;
   p.rs8 = rs;
   p.lds8 = lds;
+}
+
+// Steps that share one partial sum in the matrix-core kernel.  A step's
+// products grow with its shifts, which grow with the channels' distance from
+// the partial sum's middle; collecting a partial sum through LDS costs the
+// same whatever it spans (about three shifts' products, and half as much
+// again for the extra barrier of single steps).  With s the delay spread of
+// 16 DMs per channel, a step takes about 4.4 + 0.22 s (channels of the
+// partial sum) shifts: within 0.2 of the counted 6.4, 8.5 and 13.0 for 1, 2
+// and 4 steps of the 1024-channel beam.
+int mx_steps(const mb_plan& p) {
+  const double s = 16.0 * p.smax / std::max(p.desc.ndms - 1, 1) / p.desc.nchans;
+  int best = 1;
+  double cost = 1e30;
+  for (int ns = 1; ns <= kMxMaxSteps; ns *= 2) {
+    const double c = std::max(4.0, 4.4 + 0.22 * s * 4 * kMxCW * ns) + (ns == 1 ? 4.7 : 3.2 / ns);
+    if (c < cost) best = ns, cost = c;
+  }
+  return best;
+}
+
+// Builds the matrix-core kernel's tables on the device and decides whether
+// the plan uses it: its columns must hold the tile's outputs and the delay
+// spread of 16 DMs, its staged cells the spread of 32, and the table 16
+// shifts.  At the least tile, 128 outputs, and the most shifts it forms
+// about 25 x 10^12 adds/s by its instruction counts, against 22 for the
+// packed-add kernel at its best.
+hipError_t setup_mx(mb_plan& p) {
+  const int C = p.desc.nchans, N = p.desc.ndms, ns = mx_steps(p), G = 4 * kMxCW * ns;
+  const int nsub = (C + G - 1) / G, cpad = nsub * G, nblk = (N + kMxBD - 1) / kMxBD;
+  const size_t nstep = (size_t)nsub * ns;
+  size_t o = 0;
+  auto take = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
+  const size_t o_sb = take(4 * (size_t)nblk * cpad), o_po = take(4 * (size_t)nblk * nsub * kMxBD),
+               o_hd = take(8 * (size_t)nblk * nstep * kMxGroups * 4),
+               o_ht = take(2 * (size_t)nblk * nstep * kMxGroups * 64 * kMxCW),
+               o_mo = take(4 * (size_t)nblk * kMxBD), o_st = take(16);
+  hipError_t e = dedisp_u8_mx_prepare();
+  if (e == hipSuccess) e = hipMalloc(&p.mx_mem, o);
+  if (e != hipSuccess) return e;
+  MxSetup s{};
+  s.delays = p.d_delays;
+  s.C = C;
+  s.ndms = N;
+  s.ns = ns;
+  s.nsub = nsub;
+  s.cpad = cpad;
+  s.sbase = reinterpret_cast<int32_t*>(p.mx_mem + o_sb);
+  s.poff = reinterpret_cast<int32_t*>(p.mx_mem + o_po);
+  s.hdr = reinterpret_cast<int2*>(p.mx_mem + o_hd);
+  s.hot = reinterpret_cast<uint8_t*>(p.mx_mem + o_ht);
+  s.moff = reinterpret_cast<int32_t*>(p.mx_mem + o_mo);
+  s.stats = reinterpret_cast<int32_t*>(p.mx_mem + o_st);
+  int32_t st[4];
+  if ((e = launch_mx_setup(s, nblk, nullptr)) != hipSuccess) return e;
+  if ((e = hipMemcpy(st, s.stats, sizeof(st), hipMemcpyDeviceToHost)) != hipSuccess) return e;
+  const int BT = std::min(kMxMaxBT, std::min(kMxW - st[0], kMxCells - st[1]) & ~3);
+  p.u8_mx = BT >= kMxMinBT && st[2] <= kMxMaxShifts;
+  p.mx = MxTables{s.sbase, s.poff, s.hdr, s.hot, s.moff, cpad, nsub, ns, BT};
+  p.mx_moff = st[3];
+  if (!p.u8_mx) {
+    (void)hipFree(p.mx_mem);
+    p.mx_mem = nullptr;
+  }
+  return hipSuccess;
 }
 
 mb_status validate_rfi(const mb_rfi_params& r, int C) {
@@ -324,6 +395,8 @@ mb_status dedisp_plan_create(const mb_plan_desc* desc, mb_plan** out) {
   if (e == hipSuccess && p->u8_int) e = dedisp_u8_prepare();
   if (e == hipSuccess && p->u8_int)
     e = launch_relb_u8(p->d_delays, d.nchans, d.ndms, p->relb_ld, p->d_relb8, nullptr);
+  // a tile_hint asks for the packed-add kernel and its tiles
+  if (e == hipSuccess && p->u8_int && d.tile_hint == 0) e = setup_mx(*p);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   // the allocation-free detection's scratch address on this device, looked
   // up here so that later calls (possibly under graph capture) only read it
@@ -333,6 +406,7 @@ mb_status dedisp_plan_create(const mb_plan_desc* desc, mb_plan** out) {
     (void)hipFree(p->d_delays);
     (void)hipFree(p->d_relb);
     (void)hipFree(p->d_relb8);
+    (void)hipFree(p->mx_mem);
     delete p;
     return fail(MB_EDEVICE, "plan upload failed: %s", hipGetErrorString(e));
   }
@@ -345,6 +419,7 @@ mb_status dedisp_plan_destroy(mb_plan* plan) {
   (void)hipFree(plan->d_delays);
   (void)hipFree(plan->d_relb);
   (void)hipFree(plan->d_relb8);
+  (void)hipFree(plan->mx_mem);
   delete plan;
   return ok();
 }
@@ -659,10 +734,16 @@ mb_status dedisp_execute(const mb_plan* plan, mb_beam* beam, const void* d_in, i
     a.seen_dev = nullptr;
     a.nout = n2;
     a.out = P.d_out + n1;
-    a.rs = plan->rs8;
-    a.n_dblocks = (plan->desc.ndms + kU8BD - 1) / kU8BD;
-    a.n_ttiles = (int32_t)((n2 + kU8BT - 1) / kU8BT);
-    HIP_TRY(launch_dedisp_u8(a, plan->d_relb8, plan->lds8, s));
+    if (plan->u8_mx) {
+      a.n_dblocks = (plan->desc.ndms + kMxBD - 1) / kMxBD;
+      a.n_ttiles = (int32_t)((n2 + plan->mx_moff + plan->mx.BT - 1) / plan->mx.BT);
+      HIP_TRY(launch_dedisp_u8_mx(a, plan->mx, s));
+    } else {
+      a.rs = plan->rs8;
+      a.n_dblocks = (plan->desc.ndms + kU8BD - 1) / kU8BD;
+      a.n_ttiles = (int32_t)((n2 + kU8BT - 1) / kU8BT);
+      HIP_TRY(launch_dedisp_u8(a, plan->d_relb8, plan->lds8, s));
+    }
   } else if (P.nout > 0) {
     HIP_TRY(launch_dedisp(plan->desc.in_dtype, P.clean, ring, plan->tiling, P.a, plan->d_relb, P.fit32,
                           plan->lds, s));
