@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
@@ -864,6 +865,254 @@ __global__ __launch_bounds__(64 * NW) void dedisp_kernel(DedispArgs A, const int
                                                        dblock, ttile);
 }
 
+// Quad of a row of L samples whose first sample is q + 256 * k; quads past the
+// row's last one read as 0 (rows are readable to a multiple of 4 samples, as
+// everywhere; the split kernel's chunks have at most 2^28 samples, so byte
+// offsets fit 32 bits).
+template <typename TIN>
+__device__ inline typename Quad<TIN>::Raw quad_buffer_load(const TIN* row, uint32_t L, uint32_t q, int k) {
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<TIN*>(row), 0,
+                                                        ((L + 3u) & ~3u) * (uint32_t)sizeof(TIN), 0x00020000);
+  const int off = (int)((q + 256u * k) * (uint32_t)sizeof(TIN));
+  if constexpr (sizeof(TIN) == 4)
+    return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
+  else if constexpr (sizeof(TIN) == 2)
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, 0));
+  else
+    return __builtin_amdgcn_raw_buffer_load_b32(rsrc, off, 0, 0);
+}
+__device__ inline uint32_t flag_buffer_load(const uint8_t* flags, uint32_t L, uint32_t q, int k) {
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(flags), 0, (L + 3u) & ~3u, 0x00020000);
+  return __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)(q + 256u * k), 0, 0);
+}
+
+// Small launches: the same sums with the channels split over the waves.
+//
+// A chunk of a few hundred channels, DMs and thousands of samples has fewer
+// tiles than the GPU has compute units, and a tile of the kernel above then
+// runs its channel blocks one after the other, bound by the latency of a
+// block (load, stage, barrier: 1.0 to 1.4 us for 4 channels) and not by any
+// rate.  Here a workgroup covers kSplitDMs DMs and kSplitBT outputs, and wave
+// w takes the channel groups of kAccGroup channels w, w + nw, ...: the partial
+// sums of different groups are independent, so no wave waits for another
+// until its group is done.  Each wave stages its own rows (kSplitBC at a time,
+// the next ones in flight) in its own part of LDS, with no barrier, and
+// leaves its partials there; then each wave adds its DMs' partials in
+// ascending order.  Every addition is the tiled kernel's.
+//
+// A row feeds only eight windows, so it is staged once and read by single
+// samples, lane l taking outputs l, l + 64, ...: two per ds_read2st64_b32,
+// from any start and without conflicts, 105 bytes a clock and CU.  (Four
+// shifted copies would spend twice the reads' time on their writes; routing
+// the residues of one copy in the adds took 38 us where this takes 20.)  What
+// bounds it is the issue of a few waves' instructions, so indices, flags and
+// offsets sit one channel per lane and are read out by lane, and quads come
+// by buffer loads, which need no bounds arithmetic.
+//
+// 256 channels x 64 DMs x 8192 samples, cleaned: 63.5 -> 19.4 us; 300 channels
+// x 37 DMs x 9001 samples: 62.5 -> 21.6 us; 512 channels x 128 DMs x 8192
+// 8-bit samples, cleaned: 170 -> 56 us.
+template <typename TIN, bool CLEAN, bool RING>
+__global__ __launch_bounds__(64 * kSplitMaxWaves) void dedisp_split_kernel(DedispArgs A, const float* fit32) {
+  // rows of 8- and 16-bit data with a ring hold twice the values in flight
+  constexpr int BC = RING && sizeof(TIN) < 4 ? kSplitBC / 2 : kSplitBC;
+  constexpr int G = kSplitDMs, KM = kSplitQuads, BT = kSplitBT;
+  extern __shared__ float4 lds4[];
+  const TileIdx ti = xcd_tile(blockIdx.x, A.n_dblocks, A.n_ttiles, A.ndms % G != 0);
+  const int tid = threadIdx.x;
+  const int nw = (int)(blockDim.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  constexpr int RS = kSplitRS;
+  const int C = A.C;
+  const int d0 = ti.dblock * G;
+  const int dlast = min(d0 + G, A.ndms) - 1;
+  const int64_t t0 = (int64_t)ti.ttile * BT;
+  const int64_t vring = RING ? A.ring_valid : 0;
+  int64_t p0 = A.ring_p0;
+  if (RING && A.seen_dev != nullptr && A.R > 0) p0 = (*A.seen_dev - vring) % A.R;
+  const int32_t pv = (RING && A.R > 0) ? (int32_t)((p0 + vring) % A.R) : 0;
+  float* const part = reinterpret_cast<float*>(lds4);
+  float* const rows = part + wave * kSplitWaveFloats;  // this wave's rows, then its partials
+  const int ngroups = (C + kAccGroup - 1) / kAccGroup;
+  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 tot0 = zero4, tot1 = zero4;                   // running sums of this wave's first two DMs
+
+  for (int r0 = 0; r0 < ngroups; r0 += nw) {
+    if (r0 + wave < ngroups) {
+      const int c0 = (r0 + wave) * kAccGroup;
+      const int nch = min(kAccGroup, C - c0);
+      // Lane l holds channel c0 + l % 32: the chunk index of its window's
+      // first sample, the quads its eight windows read, per pair of DMs
+      // (lanes below 32: the even one) a window's start in the row, the 64
+      // chunk flags around it and the bandpass value.
+      const int cl = c0 + min(lane & 31, nch - 1);
+      const int base4 = A.delays[(int64_t)d0 * C + cl] & ~3;
+      const int nquads = ((A.delays[(int64_t)dlast * C + cl] - base4 + 3) >> 2) + BT / 4;
+      int off[G / 2];
+#pragma unroll
+      for (int k = 0; k < G / 2; ++k)
+        off[k] = A.delays[(int64_t)min(d0 + 2 * k + (lane >> 5), dlast) * C + cl] - base4;
+      const int32_t tw = (int32_t)(t0 - vring) + base4;
+      uint32_t m_lo = 0, m_hi = 0;
+      float fit = 0.0f;
+      if (CLEAN) {
+        const int w0 = (int)chunk_of(A.clean, max(min(tw, (int32_t)A.L), 0)) >> 5, jw = (int)A.clean.JW;
+        const uint32_t* cb = A.clean.cbits + (int64_t)cl * A.clean.JW;
+        m_lo = cb[max(min(w0, jw - 1), 0)];
+        m_hi = cb[max(min(w0 + 1, jw - 1), 0)];
+        fit = fit32[cl];
+      }
+      // Rows that lie inside the chunk with no chunk flagged: widening and
+      // the bandpass subtraction are all they need (unless a spectrum is
+      // flagged).
+      const uint32_t plain = (uint32_t)__builtin_amdgcn_ballot_w64(
+          (lane & 31) < nch && tw >= 0 && tw + 4 * nquads <= (int32_t)A.L && (m_lo | m_hi) == 0);
+      Staged<TIN, RING> st[BC][KM];
+      auto issue_rows = [&](int b) {
+#pragma unroll
+        for (int rr = 0; rr < BC; ++rr) {
+          const int i = min(b + rr, nch - 1);          // past the end: loaded, never used
+          const int c = c0 + i;
+          const int32_t t = __builtin_amdgcn_readlane(tw, i);
+          const TIN* xrow = static_cast<const TIN*>(A.x) + (int64_t)c * A.ld;
+          if constexpr (RING) {
+            const int rq = __builtin_amdgcn_readlane(nquads, i);
+#pragma unroll
+            for (int k = 0; k < KM; ++k) {
+              const int m = lane + 64 * k;
+              issue<TIN, CLEAN, RING>(st[rr][k], A, xrow, A.ring + (int64_t)c * A.R, t + 4 * m, m < rq, pv);
+            }
+          } else {
+            // buffer loads: quads past the row's end read as 0, with no
+            // index arithmetic per quad
+            const uint32_t q = (uint32_t)t + 4u * (uint32_t)lane;
+#pragma unroll
+            for (int k = 0; k < KM; ++k) {
+              st[rr][k].raw = quad_buffer_load(xrow, (uint32_t)A.L, q, k);
+              if (CLEAN) st[rr][k].g = flag_buffer_load(A.clean.gflags, (uint32_t)A.L, q, k);
+            }
+          }
+        }
+      };
+      auto write_rows = [&](int b) {
+        bool fast = ((plain >> b) & ((1u << BC) - 1)) == (1u << BC) - 1;
+        if (CLEAN) {
+          uint32_t gor = 0;
+#pragma unroll
+          for (int rr = 0; rr < BC; ++rr)
+#pragma unroll
+            for (int k = 0; k < KM; ++k) gor |= st[rr][k].g;
+          fast = fast && __builtin_amdgcn_ballot_w64(gor != 0) == 0;
+        }
+        float* const row = rows + 4 * lane;
+        if (fast) {
+#pragma unroll
+          for (int rr = 0; rr < BC; ++rr) {
+            const float f0 = CLEAN ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fit), b + rr)) : 0.0f;
+#pragma unroll
+            for (int k = 0; k < KM; ++k) {
+              float4 f;
+              if constexpr (std::is_same<TIN, float>::value) f = st[rr][k].raw;
+              else f = Quad<TIN>::widen(st[rr][k].raw);
+              if (CLEAN) { f.x -= f0; f.y -= f0; f.z -= f0; f.w -= f0; }
+              *reinterpret_cast<float4*>(row + rr * RS + 256 * k) = f;
+            }
+          }
+        } else {
+#pragma unroll
+          for (int rr = 0; rr < BC; ++rr) {
+            const int i = min(b + rr, nch - 1);
+            const int32_t t = __builtin_amdgcn_readlane(tw, i);
+            RowMeta rm;
+            rm.m_lo = __builtin_amdgcn_readlane(m_lo, i);
+            rm.m_hi = __builtin_amdgcn_readlane(m_hi, i);
+            rm.j0 = CLEAN ? ((int)chunk_of(A.clean, max(min(t, (int32_t)A.L), 0)) >> 5) * 32 : 0;
+            const float f0 = CLEAN ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fit), i)) : 0.0f;
+            // rows past the last channel read as zeros
+            const int rq = b + rr < nch ? __builtin_amdgcn_readlane(nquads, i) : 0;
+#pragma unroll
+            for (int k = 0; k < KM; ++k) {
+              const int m = lane + 64 * k;
+              *reinterpret_cast<float4*>(row + rr * RS + 256 * k) =
+                  finish<TIN, CLEAN, RING>(st[rr][k], A, rm, f0, t + 4 * m, m < rq);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        }
+      };
+      float acc[G][4] = {};
+      issue_rows(0);
+      for (int b = 0; b < nch; b += BC) {
+        write_rows(b);
+        issue_rows(b + BC);
+        asm volatile("" ::: "memory");                 // the loads stay ahead of the adds
+        // two DMs a step, the reads two steps ahead of the adds (fixed: the
+        // compiler would keep only two or three reads in flight)
+        constexpr int kSteps = BC * G / 2;
+        float v[3][2][4];
+        auto read_step = [&](int t, float (&w)[2][4]) {
+          const int rr = t / (G / 2), k = t % (G / 2);
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const float* src = rows + rr * RS + lane + __builtin_amdgcn_readlane(off[k], b + rr + 32 * e);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w[e][q] = src[64 * q];
+          }
+        };
+        read_step(0, v[0]);
+        read_step(1, v[1]);
+#pragma unroll
+        for (int t = 0; t < kSteps; ++t) {
+          if (t + 2 < kSteps) read_step(t + 2, v[(t + 2) % 3]);
+          __builtin_amdgcn_sched_barrier(0);
+          // one wait for the step's four reads instead of one for each
+          // (lgkmcnt: the reads issued after them)
+          if (t + 2 < kSteps) __builtin_amdgcn_s_waitcnt(0xC87F);
+          else if (t + 1 < kSteps) __builtin_amdgcn_s_waitcnt(0xC47F);
+          else __builtin_amdgcn_s_waitcnt(0xC07F);
+#pragma unroll
+          for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[2 * (t % (G / 2)) + e][q] += v[t % 3][e][q];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) rows[g * BT + lane + 64 * q] = acc[g][q];
+    }
+    __syncthreads();
+    // More than one round only with more than kSplitMaxWaves / 2 waves
+    // (split_waves), so a wave carries the running sums of at most two DMs.
+    const int n = min(nw, ngroups - r0);
+    const bool last = r0 + nw >= ngroups;
+    for (int g = wave; g < G; g += nw) {
+      float4 sum = r0 == 0 ? zero4 : (g == wave ? tot0 : tot1);
+      for (int w = 0; w < n; ++w) {
+        const float4 v = *reinterpret_cast<const float4*>(part + w * kSplitWaveFloats + (g * 64 + lane) * 4);
+        sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+      }
+      if (g == wave) tot0 = sum;
+      else tot1 = sum;
+      const int d = d0 + g;
+      if (!last || d > dlast) continue;
+      float* orow = A.out + (int64_t)d * A.ld_out;
+      const int64_t j = t0 + 4 * lane - A.phase;
+      if (A.phase == 0 && j + 3 < A.nout) {
+        *reinterpret_cast<float4*>(orow + j) = sum;
+      } else {
+        const float vv[4] = {sum.x, sum.y, sum.z, sum.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (j + i >= 0 && j + i < A.nout) orow[j + i] = vv[i];
+      }
+    }
+    if (!last) __syncthreads();
+  }
+}
+
 // Persistent launch over the tiles of several items (beams, chunks, plans of
 // one tiling).  Workgroups take tiles from an atomic counter in item order,
 // heaviest items first, until the counter passes the total; every
@@ -1026,6 +1275,54 @@ hipError_t launch_dedisp(int dtype, bool clean, bool ring, const Tiling& t, cons
     default: { MBTP_D(float) }
   }
 #undef MBTP_D
+}
+
+int split_waves(int C) {
+  const int groups = (C + kAccGroup - 1) / kAccGroup;
+  const int rounds = (groups + kSplitMaxWaves - 1) / kSplitMaxWaves;
+  return (groups + rounds - 1) / rounds;
+}
+
+hipError_t dedisp_split_prepare(int dtype) {
+#define MBTP_S(TIN_)                                                                  \
+  ks[0] = reinterpret_cast<const void*>(dedisp_split_kernel<TIN_, false, false>);     \
+  ks[1] = reinterpret_cast<const void*>(dedisp_split_kernel<TIN_, false, true>);      \
+  ks[2] = reinterpret_cast<const void*>(dedisp_split_kernel<TIN_, true, false>);      \
+  ks[3] = reinterpret_cast<const void*>(dedisp_split_kernel<TIN_, true, true>);
+  const void* ks[4];
+  switch (dtype) {
+    case 0: { MBTP_S(uint8_t) break; }
+    case 1: { MBTP_S(__half) break; }
+    default: { MBTP_S(float) break; }
+  }
+#undef MBTP_S
+  for (const void* k : ks) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kSplitMaxLds);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_dedisp_split(int dtype, bool clean, bool ring, const DedispArgs& a, const float* fit32,
+                               hipStream_t s) {
+  const int nw = split_waves(a.C);
+  const dim3 grid((unsigned)a.n_dblocks * (unsigned)a.n_ttiles), block((unsigned)(64 * nw));
+  const size_t lds = sizeof(float) * (size_t)nw * kSplitWaveFloats;
+#define MBTP_S(TIN_)                                                                                         \
+  if (clean) {                                                                                               \
+    if (ring) hipLaunchKernelGGL((dedisp_split_kernel<TIN_, true, true>), grid, block, lds, s, a, fit32); \
+    else hipLaunchKernelGGL((dedisp_split_kernel<TIN_, true, false>), grid, block, lds, s, a, fit32);     \
+  } else {                                                                                                   \
+    if (ring) hipLaunchKernelGGL((dedisp_split_kernel<TIN_, false, true>), grid, block, lds, s, a, fit32); \
+    else hipLaunchKernelGGL((dedisp_split_kernel<TIN_, false, false>), grid, block, lds, s, a, fit32);    \
+  }
+  switch (dtype) {
+    case 0: { MBTP_S(uint8_t) break; }
+    case 1: { MBTP_S(__half) break; }
+    default: { MBTP_S(float) break; }
+  }
+#undef MBTP_S
+  return hipGetLastError();
 }
 
 hipError_t launch_ring_update(int dtype, bool clean, const void* x, int64_t ld, int64_t L, int32_t C,

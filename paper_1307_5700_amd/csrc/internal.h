@@ -175,6 +175,24 @@ hipError_t launch_dedisp(int dtype, bool clean, bool ring, const Tiling& t, cons
                          const int32_t* relb, const float* fit32, size_t lds_bytes,
                          hipStream_t s);
 
+// Small launches (dedisp.hip): a workgroup of split_waves(C) waves covers
+// kSplitDMs DMs and kSplitBT outputs, its waves taking different groups of
+// kAccGroup channels.  A wave stages kSplitBC rows of up to kSplitRS samples
+// (kSplitQuads quads per lane); prepare raises the kernels' LDS limit.
+constexpr int kSplitDMs = 8;
+constexpr int kSplitBT = 256;
+constexpr int kSplitBC = 4;
+constexpr int kSplitQuads = 2;
+constexpr int kSplitRS = 256 * kSplitQuads;
+constexpr int kSplitMaxWaves = 16;
+constexpr int kSplitWaveFloats =
+    kSplitBC * kSplitRS > kSplitDMs * kSplitBT ? kSplitBC * kSplitRS : kSplitDMs * kSplitBT;
+constexpr int kSplitMaxLds = (int)sizeof(float) * kSplitMaxWaves * kSplitWaveFloats;
+static_assert(kSplitDMs <= 2 * (kSplitMaxWaves / 2 + 1) && kSplitMaxLds <= 160 * 1024, "split kernel");
+hipError_t dedisp_split_prepare(int dtype);
+hipError_t launch_dedisp_split(int dtype, bool clean, bool ring, const DedispArgs& a, const float* fit32,
+                               hipStream_t s);
+
 // One persistent launch over the tiles of all items (same dtype, cleaning
 // and tiling); lds = the largest item's LDS; at most grid_cap workgroups.
 hipError_t launch_dedisp_batch(int dtype, bool clean, const Tiling& t, BatchArgs& b, size_t lds,

@@ -90,6 +90,7 @@ struct mb_plan {
   int32_t* d_delays = nullptr;
   int32_t* d_relb = nullptr;
   Tiling tiling{4, 4, 2, 4, 0};
+  bool split = false;          // small launches may take the split kernel
   int tile_index = 1;          // 1-based index in the compiled list
   int rs = 0;
   size_t lds = 0;
@@ -175,6 +176,13 @@ bool tiling_fits(const Tiling& t, int rs, size_t lds) {
   }
   const int rows_per_wave = t.BC / nsw;
   return rows_per_wave * ((rs4 + 63) / 64) <= kStageQuads;
+}
+
+// Whether the split kernel's rows hold the windows of its DM blocks: a start
+// up to span + 3 samples in, kSplitBT samples, whole quads.  A tile_hint asks
+// for one of the tilings.
+bool split_fits(const mb_plan& p) {
+  return p.desc.tile_hint == 0 && ((span_max(p, kSplitDMs) + 6) & ~3) + kSplitBT <= kSplitRS;
 }
 
 mb_status choose_tiling(mb_plan& p) {
@@ -375,6 +383,7 @@ mb_status dedisp_plan_create(const mb_plan_desc* desc, mb_plan** out) {
   st = choose_tiling(*p);
   if (st) { delete p; return st; }
   u8_geometry(*p);
+  p->split = split_fits(*p);
   hipError_t e = hipGetDevice(&p->device);
   if (e != hipSuccess) { delete p; return fail(MB_EDEVICE, "hipGetDevice: %s", hipGetErrorString(e)); }
   const size_t tb = sizeof(int32_t) * p->h_delays.size();
@@ -389,6 +398,7 @@ mb_status dedisp_plan_create(const mb_plan_desc* desc, mb_plan** out) {
   }
   e = hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device);
   if (e == hipSuccess) e = dedisp_prepare(d.in_dtype, p->tiling, p->lds, p->batch_occ);
+  if (e == hipSuccess && p->split) e = dedisp_split_prepare(d.in_dtype);
   if (e == hipSuccess) e = hipMemcpy(p->d_delays, p->h_delays.data(), tb, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = launch_relb(p->d_delays, d.nchans, d.ndms, p->tiling.BD(), p->rs, p->tiling.copies(),
                                         p->relb_ld, p->d_relb, nullptr);
@@ -687,6 +697,33 @@ bool uses_u8_int(const Prepared& P) {
          (reinterpret_cast<uintptr_t>(P.d_in) & 7) == 0 && P.ld % 8 == 0;
 }
 
+// Whether a launch takes the split kernel: the plan's tiles leave compute
+// units without work, and the split kernel's smaller ones are at most four per
+// unit.  Below that line its time grows with its tiles while the tiled
+// kernel's does not (1024 channels, f32: 0.25 us a tile against 330 us for any
+// number of tiles up to one per unit; 2048 channels x 100 DMs x 16384 samples,
+// 3.1 tiles a unit: 430 against 642 us; 1024 x 200, 5.7 a unit: 357 against
+// 330 us).  With one or two channel groups there is nothing to split (32
+// channels: 17 against 11 us; 64: 18 us either way; 128: 16 against 35 us).
+// Its byte offsets hold chunks of up to 2^28 samples.
+bool takes_split(const mb_plan& p, const DedispArgs& a) {
+  const int64_t tiles = (int64_t)a.n_dblocks * a.n_ttiles;
+  const int64_t split = (int64_t)((a.ndms + kSplitDMs - 1) / kSplitDMs) * ((a.phase + a.nout + kSplitBT - 1) / kSplitBT);
+  return p.split && a.C > 2 * kAccGroup && a.L <= (int64_t(1) << 28) && tiles <= p.cus && split <= 4 * (int64_t)p.cus;
+}
+
+// One launch of the float kernels.
+hipError_t launch_float(const mb_plan& p, bool clean, bool ring, const DedispArgs& a, const float* fit32,
+                        hipStream_t s) {
+  if (takes_split(p, a)) {
+    DedispArgs b = a;
+    b.n_dblocks = (p.desc.ndms + kSplitDMs - 1) / kSplitDMs;
+    b.n_ttiles = (int32_t)((a.phase + a.nout + kSplitBT - 1) / kSplitBT);
+    return launch_dedisp_split(p.desc.in_dtype, clean, ring, b, fit32, s);
+  }
+  return launch_dedisp(p.desc.in_dtype, clean, ring, p.tiling, a, p.d_relb, fit32, p.lds, s);
+}
+
 // Normalisation and ring update of a prepared item, after its dedispersion.
 mb_status finish_item(Prepared& P, hipStream_t s) {
   const mb_plan* plan = P.plan;
@@ -723,7 +760,7 @@ mb_status dedisp_execute(const mb_plan* plan, mb_beam* beam, const void* d_in, i
       DedispArgs a = P.a;
       a.nout = n1;
       a.n_ttiles = (int32_t)((a.phase + n1 + plan->tiling.BT() - 1) / plan->tiling.BT());
-      HIP_TRY(launch_dedisp(plan->desc.in_dtype, false, true, plan->tiling, a, plan->d_relb, P.fit32, plan->lds, s));
+      HIP_TRY(launch_float(*plan, false, true, a, P.fit32, s));
     }
     DedispArgs a = P.a;
     a.ring = nullptr;
@@ -745,8 +782,7 @@ mb_status dedisp_execute(const mb_plan* plan, mb_beam* beam, const void* d_in, i
       HIP_TRY(launch_dedisp_u8(a, plan->d_relb8, plan->lds8, s));
     }
   } else if (P.nout > 0) {
-    HIP_TRY(launch_dedisp(plan->desc.in_dtype, P.clean, ring, plan->tiling, P.a, plan->d_relb, P.fit32,
-                          plan->lds, s));
+    HIP_TRY(launch_float(*plan, P.clean, ring, P.a, P.fit32, s));
   }
   st = finish_item(P, s);
   if (st) return st;
