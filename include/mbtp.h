@@ -158,12 +158,18 @@ typedef struct {
   int32_t reserved;
 } mb_peak;
 
+/* Dedispersion kernels, as flags of mb_exec_info.kernels: the float kernel in
+ * tiles of the plan's tiling, the float kernel that splits channel groups over
+ * waves, the packed 16-bit add kernel and the matrix-core kernel (both exact
+ * integers, for 8-bit samples). */
+enum { MB_KERNEL_TILED = 1, MB_KERNEL_SPLIT = 2, MB_KERNEL_PACKED8 = 4, MB_KERNEL_MATRIX8 = 8 };
+
 /* Streaming position of a beam after an execute (host-known). */
 typedef struct {
   int64_t nout;      /* dedispersed samples produced per DM by this call   */
   int64_t sample0;   /* absolute index of the first of them                */
-  int32_t integer_kernel; /* 1 when the exact integer kernel dedispersed it */
-  int32_t reserved;
+  int32_t integer_kernel; /* 1 when an exact integer kernel dedispersed it */
+  int32_t kernels;   /* MB_KERNEL_* flags of the kernels that formed them  */
 } mb_exec_info;
 
 typedef struct mb_plan mb_plan;

@@ -66,9 +66,11 @@ class StepItem(ctypes.Structure):
 
 
 class ExecInfo(ctypes.Structure):
-    _fields_ = [("nout", c_i64), ("sample0", c_i64), ("integer_kernel", c_i32), ("reserved", c_i32)]
+    _fields_ = [("nout", c_i64), ("sample0", c_i64), ("integer_kernel", c_i32), ("kernels", c_i32)]
 
 
+# MB_KERNEL_*: flags of ExecInfo.kernels
+KERNELS = {"tiled": 1, "split": 2, "packed8": 4, "matrix8": 8}
 DETECT_NOALLOC_MAX_DMS = 8192   # MB_DETECT_NOALLOC_MAX_DMS
 NORM_BYTES = 32        # mb_norm: 3 doubles + 2 int32
 CANDIDATE_BYTES = 24   # mb_candidate

@@ -79,7 +79,8 @@ class Plan:
         self.tiling = dict(index=info.tile_index, waves=info.waves, dm_block=info.dm_block,
                            time_tile=info.time_tile, chan_block=info.chan_block,
                            lds_bytes=info.lds_bytes, u8_integer=bool(info.u8_integer))
-        self.last_integer_kernel = False   # whether the last execute ran the exact integer kernel
+        self.last_integer_kernel = False   # whether the last execute ran an exact integer kernel
+        self._kernels = 0
         self.dm_start, self.dm_step = float(dm_start), float(dm_step)
         ws = ctypes.c_size_t()
         L.check(L.lib().detect_workspace_size(h, ctypes.byref(ws)), "detect_workspace_size")
@@ -89,6 +90,11 @@ class Plan:
     def from_beam(cls, beam, rfi: RfiConfig | None = None, tile_hint: int = 0, device=None):
         return cls(dtype=beam.dtype, rfi=rfi, tile_hint=tile_hint, device=device,
                    **beam.plan_kwargs())
+
+    @property
+    def last_kernels(self) -> tuple:
+        """Names (_lib.KERNELS) of the dedispersion kernels that the last execute ran."""
+        return tuple(k for k, bit in L.KERNELS.items() if self._kernels & bit)
 
     # ---- plan ----
     def delays(self) -> np.ndarray:
@@ -203,6 +209,7 @@ class Plan:
             if norm is not None:
                 self.normalise(out, info.nout, norm, stream=stream)
         self.last_integer_kernel = bool(info.integer_kernel)
+        self._kernels = info.kernels
         return out, norm, info.nout, info.sample0
 
     def normalise(self, out: torch.Tensor, nout: int, norm: torch.Tensor | None = None, stream=None):

@@ -717,15 +717,17 @@ bool takes_split(const mb_plan& p, bool ring, const DedispArgs& a) {
   return p.split && a.C > 2 * kAccGroup && a.L <= (int64_t(1) << 28) && tiles <= p.cus && split <= per_unit * p.cus;
 }
 
-// One launch of the float kernels.
+// One launch of the float kernels; adds the one it takes to `kernels`.
 hipError_t launch_float(const mb_plan& p, bool clean, bool ring, const DedispArgs& a, const float* fit32,
-                        hipStream_t s) {
+                        hipStream_t s, int32_t& kernels) {
   if (takes_split(p, ring, a)) {
+    kernels |= MB_KERNEL_SPLIT;
     DedispArgs b = a;
     b.n_dblocks = (p.desc.ndms + kSplitDMs - 1) / kSplitDMs;
     b.n_ttiles = (int32_t)((a.phase + a.nout + kSplitBT - 1) / kSplitBT);
     return launch_dedisp_split(p.desc.in_dtype, clean, ring, b, fit32, s);
   }
+  kernels |= MB_KERNEL_TILED;
   return launch_dedisp(p.desc.in_dtype, clean, ring, p.tiling, a, p.d_relb, fit32, p.lds, s);
 }
 
@@ -755,6 +757,7 @@ mb_status dedisp_execute(const mb_plan* plan, mb_beam* beam, const void* d_in, i
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool ring = beam != nullptr && P.a.ring_valid > 0;
   const bool integer = P.nout > 0 && uses_u8_int(P);
+  int32_t kernels = 0;
   if (integer) {
     // The last nsamps - s_max outputs read only this chunk's samples: the
     // integer kernel sums them as a single shot over the chunk.  With ring
@@ -765,7 +768,7 @@ mb_status dedisp_execute(const mb_plan* plan, mb_beam* beam, const void* d_in, i
       DedispArgs a = P.a;
       a.nout = n1;
       a.n_ttiles = (int32_t)((a.phase + n1 + plan->tiling.BT() - 1) / plan->tiling.BT());
-      HIP_TRY(launch_float(*plan, false, true, a, P.fit32, s));
+      HIP_TRY(launch_float(*plan, false, true, a, P.fit32, s, kernels));
     }
     DedispArgs a = P.a;
     a.ring = nullptr;
@@ -777,17 +780,19 @@ mb_status dedisp_execute(const mb_plan* plan, mb_beam* beam, const void* d_in, i
     a.nout = n2;
     a.out = P.d_out + n1;
     if (plan->u8_mx) {
+      kernels |= MB_KERNEL_MATRIX8;
       a.n_dblocks = (plan->desc.ndms + kMxBD - 1) / kMxBD;
       a.n_ttiles = (int32_t)((n2 + plan->mx_moff + plan->mx.BT - 1) / plan->mx.BT);
       HIP_TRY(launch_dedisp_u8_mx(a, plan->mx, s));
     } else {
+      kernels |= MB_KERNEL_PACKED8;
       a.rs = plan->rs8;
       a.n_dblocks = (plan->desc.ndms + kU8BD - 1) / kU8BD;
       a.n_ttiles = (int32_t)((n2 + kU8BT - 1) / kU8BT);
       HIP_TRY(launch_dedisp_u8(a, plan->d_relb8, plan->lds8, s));
     }
   } else if (P.nout > 0) {
-    HIP_TRY(launch_float(*plan, P.clean, ring, P.a, P.fit32, s));
+    HIP_TRY(launch_float(*plan, P.clean, ring, P.a, P.fit32, s, kernels));
   }
   st = finish_item(P, s);
   if (st) return st;
@@ -795,7 +800,7 @@ mb_status dedisp_execute(const mb_plan* plan, mb_beam* beam, const void* d_in, i
     info->nout = P.nout;
     info->sample0 = P.sample0;
     info->integer_kernel = integer ? 1 : 0;
-    info->reserved = 0;
+    info->kernels = kernels;
   }
   return ok();
 }
@@ -871,7 +876,7 @@ mb_status dedisp_execute_batch(const mb_batch_item* items, int32_t nitems, void*
       infos[i].nout = P[i].nout;
       infos[i].sample0 = P[i].sample0;
       infos[i].integer_kernel = 0;
-      infos[i].reserved = 0;
+      infos[i].kernels = P[i].nout > 0 ? MB_KERNEL_TILED : 0;
     }
   }
   return ok();
@@ -1150,7 +1155,7 @@ mb_status detect_candidates_noalloc(const mb_plan* plan, const float* d_out, int
 struct mb_step_graph {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
-  struct Item { mb_beam* beam; int64_t nsamps, nout, sample0; int32_t integer_kernel; };
+  struct Item { mb_beam* beam; int64_t nsamps, nout, sample0; int32_t integer_kernel, kernels; };
   std::vector<Item> items;
 };
 
@@ -1236,7 +1241,7 @@ mb_status dedisp_step_graph_create(const mb_step_item* items, int32_t nitems, vo
   g->graph = graph;
   for (int32_t i = 0; i < nitems; ++i)
     g->items[i] = mb_step_graph::Item{items[i].beam, items[i].nsamps, infos[i].nout, infos[i].sample0,
-                                      infos[i].integer_kernel};
+                                      infos[i].integer_kernel, infos[i].kernels};
   *out = g;
   return ok();
 }
@@ -1252,7 +1257,7 @@ mb_status dedisp_step_graph_launch(mb_step_graph* graph, void* stream, mb_exec_i
       s0 = it.beam->base + it.beam->seen - it.beam->plan->smax;
       it.beam->seen += it.nsamps;
     }
-    if (infos) infos[i] = mb_exec_info{it.nout, s0, it.integer_kernel, 0};
+    if (infos) infos[i] = mb_exec_info{it.nout, s0, it.integer_kernel, it.kernels};
   }
   return ok();
 }
