@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "mx_rule.h"
+
 namespace mbtp {
 
 // Four FP32 lanes as a clang vector: the operand type of 16-byte
@@ -226,7 +228,8 @@ hipError_t launch_dedisp_u8(const DedispArgs& a, const int32_t* relb, size_t lds
 // kMxCW channels, kMxCells of them per quarter of a step.
 constexpr int kMxJ = 9, kMxPieces = 4, kMxGroups = 2, kMxBD = 16 * kMxGroups;
 constexpr int kMxW = 16 * kMxJ * kMxPieces, kMxMaxBT = 512, kMxMinBT = 128;
-constexpr int kMxCW = 16, kMxCells = 684, kMxMaxSteps = 8, kMxMaxShifts = 16;
+constexpr int kMxCW = 16, kMxCells = 684, kMxMaxShifts = 16;
+static_assert(kMxStepChans == 4 * kMxCW, "a step is four cells");
 constexpr int kMxLds = 2 * 4 * kMxCells * kMxCW + 4 * (kMxBD * (kMxW + 4) + 512);
 static_assert(kMxLds <= 160 * 1024, "LDS of a CU");
 // Tables of a plan, steps numbered over all partial sums.

@@ -223,25 +223,6 @@ void u8_geometry(mb_plan& p) {
   p.lds8 = lds;
 }
 
-// Steps that share one partial sum in the matrix-core kernel.  A step's
-// products grow with its shifts, which grow with the channels' distance from
-// the partial sum's middle; collecting a partial sum through LDS costs the
-// same whatever it spans (about three shifts' products, and half as much
-// again for the extra barrier of single steps).  With s the delay spread of
-// 16 DMs per channel, a step takes about 4.4 + 0.22 s (channels of the
-// partial sum) shifts: within 0.2 of the counted 6.4, 8.5 and 13.0 for 1, 2
-// and 4 steps of the 1024-channel beam.
-int mx_steps(const mb_plan& p) {
-  const double s = 16.0 * p.smax / std::max(p.desc.ndms - 1, 1) / p.desc.nchans;
-  int best = 1;
-  double cost = 1e30;
-  for (int ns = 1; ns <= kMxMaxSteps; ns *= 2) {
-    const double c = std::max(4.0, 4.4 + 0.22 * s * 4 * kMxCW * ns) + (ns == 1 ? 4.7 : 3.2 / ns);
-    if (c < cost) best = ns, cost = c;
-  }
-  return best;
-}
-
 // Builds the matrix-core kernel's tables on the device and decides whether
 // the plan uses it: its columns must hold the tile's outputs and the delay
 // spread of 16 DMs, its staged cells the spread of 32, and the table 16
@@ -249,8 +230,8 @@ int mx_steps(const mb_plan& p) {
 // about 25 x 10^12 adds/s by its instruction counts, against 22 for the
 // packed-add kernel at its best.
 hipError_t setup_mx(mb_plan& p) {
-  const int C = p.desc.nchans, N = p.desc.ndms, ns = mx_steps(p), G = 4 * kMxCW * ns;
-  const int nsub = (C + G - 1) / G, cpad = nsub * G, nblk = (N + kMxBD - 1) / kMxBD;
+  const int C = p.desc.nchans, N = p.desc.ndms, ns = mx_steps(mx_spread(p.h_delays.data(), N, C), C);
+  const int nsub = mx_padded_steps(C, ns) / ns, cpad = nsub * ns * kMxStepChans, nblk = (N + kMxBD - 1) / kMxBD;
   const size_t nstep = (size_t)nsub * ns;
   size_t o = 0;
   auto take = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
