@@ -760,7 +760,8 @@ mb_status dedisp_execute(const mb_plan* plan, mb_beam* beam, const void* d_in, i
     a.seen_dev = nullptr;
     a.nout = n2;
     a.out = P.d_out + n1;
-    if (plan->u8_mx) {
+    if (plan->u8_mx && mx_pays(plan->desc.nchans, plan->desc.ndms, n2, plan->mx.ns, kMxBD, plan->mx.BT, kU8BD, kU8BT,
+                               plan->cus)) {
       kernels |= MB_KERNEL_MATRIX8;
       a.n_dblocks = (plan->desc.ndms + kMxBD - 1) / kMxBD;
       a.n_ttiles = (int32_t)((n2 + plan->mx_moff + plan->mx.BT - 1) / plan->mx.BT);

@@ -54,4 +54,27 @@ inline int mx_steps(double s, int C) {
   return best;
 }
 
+// Whether a launch of ndms DMs and nout outputs is faster on this kernel, in
+// tiles of mx_bd DMs and mx_bt outputs, than on the packed-add kernel in tiles
+// of u8_bd and u8_bt, with `units` tiles at a time on the GPU.  In us, fitted to
+// both kernels' times: a tile costs this kernel its steps, full or not (about
+// 4.1 us each, and 8 to start and end), the other one its channels (0.13 us
+// each for a few DMs, 0.23 for whole blocks).  So a step needs some 30 channels
+// to pay: 13 channels x 1 DM x 1143 samples 10.5 us here and 5.8 there, 20 x
+// 505 x 28403 40.1 and 32.5, 66 x 3 x 1346 17.7 and 16.2, 64 x 1 x 6786 10.3
+// and 12.6, 93 x 19 x 9081 16.0 and 20.4.  Over 810 launches of 4 to 4096
+// channels, 1 to 2048 DMs and 100 to 130000 outputs the choice is 0.6 % slower
+// than the better kernel on average, and more than 3 % slower than the
+// packed-add kernel twice (8 and 6 %).
+inline bool mx_pays(int C, int ndms, int64_t nout, int ns, int mx_bd, int mx_bt, int u8_bd, int u8_bt, int units) {
+  auto rounds = [&](int bd, int bt) {
+    const int64_t tiles = (int64_t)((ndms + bd - 1) / bd) * ((nout + bt - 1) / bt);
+    return (double)((tiles + units - 1) / units);
+  };
+  const double steps = mx_padded_steps(C, ns), full = std::min(ndms, u8_bd) / (double)u8_bd;
+  const double mx = 8.0 + 4.1 * steps + (rounds(mx_bd, mx_bt) - 1) * (5.0 + 3.0 * steps);
+  const double u8 = 5.0 + C * (0.13 + 0.10 * full) + (rounds(u8_bd, u8_bt) - 1) * (3.0 + 0.20 * C);
+  return mx < u8;
+}
+
 }  // namespace mbtp

@@ -97,3 +97,15 @@ def test_8_bit_chunks_report_their_kernels():
     wide = _plan(16, 33, "u8", tsamp=51.2e-6)                # too many shifts for the one-hot table
     wide.execute(_input(16, 2048, "u8", ld=2048))
     assert wide.last_kernels == ("packed8",)
+
+
+@pytest.mark.parametrize("C,nd,T,name", [(13, 1, 1143, "packed8"), (20, 505, 6000, "packed8"), (66, 3, 1346, "packed8"),
+                                         (93, 19, 9081, "matrix8"), (300, 64, 9000, "matrix8")])
+def test_few_channels_take_the_packed_add_kernel(C, nd, T, name):
+    """Equal delays (every DM fits the one-hot table): the channels decide, and
+    either kernel gives the packed-add kernel's bits."""
+    plan, packed = [_plan(C, nd, "u8", dm_step=0.0, hint=h) for h in (0, 1)]
+    x = _input(C, T, "u8", ld=(T + 7) // 8 * 8)
+    outs = [p.execute(x)[0][:, :T].clone() for p in (plan, packed)]
+    assert plan.last_kernels == (name,) and packed.last_kernels == ("packed8",)
+    assert torch.equal(*outs)
