@@ -384,10 +384,12 @@ __global__ __launch_bounds__(64 * kWaves) void dedisp_u8_mx_kernel(DedispArgs A,
   }
 }
 
-// Tables of one plan: one workgroup per (partial sum, DM block).
+// Statistics and, where there is room for them, tables of one plan: one
+// workgroup per (partial sum, DM block).
 __global__ __launch_bounds__(256) void mx_setup_kernel(MxSetup P) {
   const int sub = blockIdx.x, blk = blockIdx.y, tid = threadIdx.x;
   const int C = P.C, ns = P.ns, G = ns * kCS, nstep = P.nsub * ns, ncell = 4 * ns;
+  const bool tables = P.hdr != nullptr;
   const int d0 = blk * kBD, dc = d0 + min(kBD, P.ndms - d0) / 2;       // the block's middle DM
   const int mid = C / 2, ref = min(sub * G + G / 2, C - 1);
   constexpr int kNone = 0x3fffffff;
@@ -443,19 +445,19 @@ __global__ __launch_bounds__(256) void mx_setup_kernel(MxSetup P) {
     for (int q = 0; q < 4; ++q) {
       const int cell = 4 * st + q;
       const int off = emin[g] - ymin + (lo[cell] < kNone ? amin[cell][g] - lo[cell] : 0);
-      P.hdr[(((int64_t)blk * nstep + sub * ns + st) * kGroups + g) * 4 + q] = make_int2(off, S);
+      if (tables) P.hdr[(((int64_t)blk * nstep + sub * ns + st) * kGroups + g) * 4 + q] = make_int2(off, S);
       atomicMax(&need, off + spread[g] + S);
     }
     atomicMax(&P.stats[2], S);
   }
-  for (int i = tid; i < G; i += 256) {
+  for (int i = tid; tables && i < G; i += 256) {
     const int cell = i / kCW;
     const int c = min(cell_channel(sub, cell / 4, cell % 4, ns) + i % kCW, C - 1);
     P.sbase[(int64_t)blk * P.cpad + sub * G + i] =
         mlo + ymin + (del(dc, c) - del(dc, ref)) + (lo[cell] < kNone ? lo[cell] : 0);
   }
   const int64_t half = (int64_t)gridDim.y * nstep * kGroups * 64 * kCW;
-  for (int i = tid; i < ns * kGroups * 64 * kCW; i += 256) {
+  for (int i = tid; tables && i < ns * kGroups * 64 * kCW; i += 256) {
     const int ch = i % kCW, lane = (i / kCW) % 64, g = (i / kCW / 64) % kGroups, st = i / kCW / 64 / kGroups;
     const int cell = 4 * st + (lane >> 4), c = cell_channel(sub, st, lane >> 4, ns) + ch;
     const int q = c < C ? rel(d0 + 16 * g + (lane & 15), c) - amin[cell][g] : -1;
@@ -465,10 +467,10 @@ __global__ __launch_bounds__(256) void mx_setup_kernel(MxSetup P) {
   }
   if (tid < kBD) {
     const int po = e[tid] - emin[tid / 16];
-    P.poff[((int64_t)blk * P.nsub + sub) * kBD + tid] = po;
+    if (tables) P.poff[((int64_t)blk * P.nsub + sub) * kBD + tid] = po;
     atomicMax(&P.stats[0], po);
     if (sub == 0) {
-      P.moff[d0 + tid] = m[tid] - mlo;
+      if (tables) P.moff[d0 + tid] = m[tid] - mlo;
       atomicMax(&P.stats[3], mhi - mlo);
     }
   }

@@ -243,6 +243,8 @@ struct MxTables {
   int32_t cpad, nsub, ns;    // padded channels; partial sums; steps of a partial sum
   int32_t BT;                // outputs of a tile
 };
+// Setup of one plan's tables; with no tables (null pointers) only the
+// statistics that say whether its delays fit.
 struct MxSetup {
   const int32_t* delays;
   int32_t C, ndms, ns, nsub, cpad;

@@ -103,7 +103,7 @@ struct mb_plan {
   bool u8_int = false;
   int rs8 = 0;
   size_t lds8 = 0;
-  int32_t* d_relb8 = nullptr;
+  int32_t* d_relb8 = nullptr;  // and behind them the statistics of setup_mx
   // and its matrix-core form, when the delays fit that kernel's tile: one
   // device allocation with the tables
   bool u8_mx = false;
@@ -223,50 +223,60 @@ void u8_geometry(mb_plan& p) {
   p.lds8 = lds;
 }
 
-// Builds the matrix-core kernel's tables on the device and decides whether
-// the plan uses it: its columns must hold the tile's outputs and the delay
-// spread of 16 DMs, its staged cells the spread of 32, and the table 16
-// shifts.  At the least tile, 128 outputs, and the most shifts it forms
-// about 25 x 10^12 adds/s by its instruction counts, against 22 for the
-// packed-add kernel at its best.
+// Decides whether the plan uses the matrix-core kernel and builds its tables on
+// the device: its columns must hold the tile's outputs and the delay spread of
+// 16 DMs, its staged cells the spread of 32, and the table 16 shifts (at the
+// least tile, 128 outputs, and the most shifts it forms about 25 x 10^12 adds/s
+// by its instruction counts, against 22 for the packed-add kernel at its best).
+// The tables take 2 bytes per DM and channel, so what the delays need is found
+// first; a plan whose tables do not fit in memory keeps the packed-add kernel.
 hipError_t setup_mx(mb_plan& p) {
-  const int C = p.desc.nchans, N = p.desc.ndms, ns = mx_steps(mx_spread(p.h_delays.data(), N, C), C);
-  const int nsub = mx_padded_steps(C, ns) / ns, cpad = nsub * ns * kMxStepChans, nblk = (N + kMxBD - 1) / kMxBD;
-  const size_t nstep = (size_t)nsub * ns;
-  size_t o = 0;
-  auto take = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
-  const size_t o_sb = take(4 * (size_t)nblk * cpad), o_po = take(4 * (size_t)nblk * nsub * kMxBD),
-               o_hd = take(8 * (size_t)nblk * nstep * kMxGroups * 4),
-               o_ht = take(2 * (size_t)nblk * nstep * kMxGroups * 64 * kMxCW),
-               o_mo = take(4 * (size_t)nblk * kMxBD), o_st = take(16);
+  const int C = p.desc.nchans, N = p.desc.ndms, nblk = (N + kMxBD - 1) / kMxBD;
   hipError_t e = dedisp_u8_mx_prepare();
-  if (e == hipSuccess) e = hipMalloc(&p.mx_mem, o);
   if (e != hipSuccess) return e;
   MxSetup s{};
   s.delays = p.d_delays;
   s.C = C;
   s.ndms = N;
-  s.ns = ns;
-  s.nsub = nsub;
-  s.cpad = cpad;
-  s.sbase = reinterpret_cast<int32_t*>(p.mx_mem + o_sb);
-  s.poff = reinterpret_cast<int32_t*>(p.mx_mem + o_po);
-  s.hdr = reinterpret_cast<int2*>(p.mx_mem + o_hd);
-  s.hot = reinterpret_cast<uint8_t*>(p.mx_mem + o_ht);
-  s.moff = reinterpret_cast<int32_t*>(p.mx_mem + o_mo);
-  s.stats = reinterpret_cast<int32_t*>(p.mx_mem + o_st);
-  int32_t st[4];
-  if ((e = launch_mx_setup(s, nblk, nullptr)) != hipSuccess) return e;
-  if ((e = hipMemcpy(st, s.stats, sizeof(st), hipMemcpyDeviceToHost)) != hipSuccess) return e;
-  const int BT = std::min(kMxMaxBT, std::min(kMxW - st[0], kMxCells - st[1]) & ~3);
-  p.u8_mx = BT >= kMxMinBT && st[2] <= kMxMaxShifts;
-  p.mx = MxTables{s.sbase, s.poff, s.hdr, s.hot, s.moff, cpad, nsub, ns, BT};
-  p.mx_moff = st[3];
-  if (!p.u8_mx) {
-    (void)hipFree(p.mx_mem);
-    p.mx_mem = nullptr;
+  s.stats = p.d_relb8 + (size_t)p.relb_ld * N;
+  int BT = 0;
+  int32_t st[4] = {0, 0, 0, 0};
+  bool fits = false;
+  // longer partial sums need more shifts: where they are too many, shorter ones
+  for (int ns = mx_steps(mx_spread(p.h_delays.data(), N, C), C); ns >= 1 && !fits; ns /= 2) {
+    s.ns = ns;
+    s.nsub = mx_padded_steps(C, ns) / ns;
+    s.cpad = s.nsub * ns * kMxStepChans;
+    e = launch_mx_setup(s, nblk, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(st, s.stats, sizeof(st), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) break;
+    BT = std::min(kMxMaxBT, std::min(kMxW - st[0], kMxCells - st[1]) & ~3);
+    fits = BT >= kMxMinBT && st[2] <= kMxMaxShifts;
   }
-  return hipSuccess;
+  if (e == hipSuccess && fits) {
+    const size_t nstep = (size_t)s.nsub * s.ns;
+    size_t o = 0;
+    auto take = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
+    const size_t o_sb = take(4 * (size_t)nblk * s.cpad), o_po = take(4 * (size_t)nblk * s.nsub * kMxBD),
+                 o_hd = take(8 * (size_t)nblk * nstep * kMxGroups * 4),
+                 o_ht = take(2 * (size_t)nblk * nstep * kMxGroups * 64 * kMxCW),
+                 o_mo = take(4 * (size_t)nblk * kMxBD);
+    if (hipMalloc(&p.mx_mem, o) == hipSuccess) {
+      s.sbase = reinterpret_cast<int32_t*>(p.mx_mem + o_sb);
+      s.poff = reinterpret_cast<int32_t*>(p.mx_mem + o_po);
+      s.hdr = reinterpret_cast<int2*>(p.mx_mem + o_hd);
+      s.hot = reinterpret_cast<uint8_t*>(p.mx_mem + o_ht);
+      s.moff = reinterpret_cast<int32_t*>(p.mx_mem + o_mo);
+      e = launch_mx_setup(s, nblk, nullptr);
+      p.u8_mx = true;
+      p.mx = MxTables{s.sbase, s.poff, s.hdr, s.hot, s.moff, s.cpad, s.nsub, s.ns, BT};
+      p.mx_moff = st[3];
+    } else {
+      p.mx_mem = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  return e;
 }
 
 mb_status validate_rfi(const mb_rfi_params& r, int C) {
@@ -371,7 +381,7 @@ mb_status dedisp_plan_create(const mb_plan_desc* desc, mb_plan** out) {
   p->relb_ld = (d.nchans + 3) & ~3;
   const size_t rb = sizeof(int32_t) * (size_t)p->relb_ld * d.ndms;
   if (hipMalloc(&p->d_delays, tb) != hipSuccess || hipMalloc(&p->d_relb, rb) != hipSuccess ||
-      (p->u8_int && hipMalloc(&p->d_relb8, rb) != hipSuccess)) {
+      (p->u8_int && hipMalloc(&p->d_relb8, rb + 4 * sizeof(int32_t)) != hipSuccess)) {
     (void)hipFree(p->d_delays);
     (void)hipFree(p->d_relb);
     delete p;
