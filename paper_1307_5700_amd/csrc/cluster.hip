@@ -764,6 +764,7 @@ hipError_t launch_fdbscan(const CandDev* c, int32_t n, int32_t ndms, int64_t t_e
   int32_t* queue = reinterpret_cast<int32_t*>(w);
   w += up(4 * (size_t)n);
   uint64_t* keys = reinterpret_cast<uint64_t*>(w);
+  dm_eps = std::min(dm_eps, std::max(ndms - 1, 0));   // no two rows lie further apart
   ClusterArgs A{c, n, ndms, dm_eps, t_eps, snr_eps, min_pts, row_start};
   const unsigned gn = (unsigned)((n + 255) / 256);
   const int64_t rows_threads = (int64_t)n * (2 * (int64_t)dm_eps + 1);
