@@ -370,13 +370,24 @@ __device__ inline void fdb_join_row(const ClusterArgs& A, const CandDev& p, int3
 // Dependent loads bound it (about 400 clocks each), so the chains are short
 // and overlap: which points a cluster expands follows from representatives
 // and query marks alone, so one wave follows those from level to level, with
-// no barrier, while the other 15 join the members of the neighbourhoods of
-// the points it has queued, kFdbGroup lanes to a point and DM row; the scan
-// for the next start takes kFdbScan points a thread at a time, one barrier a
-// step (its minimum rotates over three slots, the next one cleared while this
-// one is in use).  53 858 detections, 640 DM rows, 5 pulses (27 clusters, 111
+// no barrier, while the other 15 (and it, once done) join the members of the
+// neighbourhoods of the points it has queued, kFdbGroup lanes to a point and DM
+// row; the scan for the next start takes kFdbScan points a thread at a time, one
+// barrier a step (its minimum rotates over three slots, the next one cleared
+// while this one is in use).  53 858 detections, 640 DM rows, 5 pulses (27 clusters, 111
 // levels, 1532 points expanded): 837 -> 374 us.
+//
+// Groups keep few rows in flight, which is enough while the joins follow the
+// levels; with wide neighbourhoods (a large dm_eps) they fall behind, and from
+// kFdbBacklog waiting rows on a wave takes 64 of them, one to a lane: a row takes
+// longer there, but eight times as many are under way.  15048 detections in 640 DM rows, all rows in reach, 120 -> 27.9 ms; 2390 in 64
+// rows, all in reach, 1.34 -> 1.00 ms (limits of 128, 512 and 1024 rows: 0.96,
+// 1.11 and 1.15 ms); with few rows in reach as before.  Runs of hundreds of
+// points are slower so: 2390 in 64 rows, 9 rows of 8001 samples in reach, 0.30 ->
+// 0.36 ms.
 constexpr int kFdbScan = 4;
+constexpr int kFdbItems = 64 / kFdbGroup;
+constexpr int kFdbBacklog = 256;
 
 __global__ __launch_bounds__(1024) void fdb_expand_kernel(ClusterArgs A, const int32_t* __restrict__ cnt,
                                                           const uint64_t* __restrict__ keys,
@@ -388,6 +399,7 @@ __global__ __launch_bounds__(1024) void fdb_expand_kernel(ClusterArgs A, const i
   // what the expanding wave publishes: points queued so far (each index at
   // most once), and the number of clusters expanded to their end
   __shared__ int32_t s_queued, s_ended;
+  __shared__ unsigned long long s_taken;          // (point, DM row) items of the cluster that joining waves took
   const int tid = threadIdx.x, lane = tid & 63, gl = lane & (kFdbGroup - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t n = A.n;
@@ -439,6 +451,7 @@ __global__ __launch_bounds__(1024) void fdb_expand_kernel(ClusterArgs A, const i
     if (tid == 0) {
       queried[first] = 1;
       queue[q0] = first;
+      s_taken = 0;
     }
     __syncthreads();
     if (wave == 0) {
@@ -478,28 +491,44 @@ __global__ __launch_bounds__(1024) void fdb_expand_kernel(ClusterArgs A, const i
       }
       __builtin_amdgcn_s_setprio(0);
       if (lane == 0) __hip_atomic_store(&s_ended, ncl, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-    } else {
-      // every member of their neighbourhoods that carries no label joins the
-      // cluster (all writers write cid): one (point, DM row) item a group,
-      // as the items come; the expanding wave waits for nothing, so its end
-      // always comes
-      constexpr int kItems = 64 / kFdbGroup;
-      for (int64_t item = (int64_t)(wave - 1) * kItems;; item += 15 * kItems) {
-        int64_t items;
-        bool ended;
-        for (;;) {
-          ended = __hip_atomic_load(&s_ended, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == ncl;
-          items = (__hip_atomic_load(&s_queued, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) - q0) * R;
-          if (ended || items >= item + kItems) break;
-          __builtin_amdgcn_s_sleep(1);
-        }
-        if (item >= items) break;                 // ended, none left
-        const int64_t t = item + lane / kFdbGroup;
-        if (t >= items) continue;
+    }
+    // every member of their neighbourhoods that carries no label joins the
+    // cluster (all writers write cid): (point, DM row) items, as they come; the
+    // expanding wave waits for nothing, so its end always comes, and then it
+    // joins the rest with the others
+    for (;;) {
+      // a wave takes as many items as it has groups, or lanes
+      int64_t items = (__hip_atomic_load(&s_queued, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) - q0) * R;
+      int64_t item = 0;
+      int take = kFdbItems;
+      if (lane == 0) {
+        const int64_t taken = (int64_t)__hip_atomic_load(&s_taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (items - taken >= kFdbBacklog) take = 64;
+        item = (int64_t)atomicAdd(&s_taken, (unsigned long long)take);
+      }
+      take = __builtin_amdgcn_readfirstlane(take);
+      item = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(item >> 32)) << 32) |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)item));
+      for (;;) {
+        const bool ended = __hip_atomic_load(&s_ended, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == ncl;
+        items = (__hip_atomic_load(&s_queued, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) - q0) * R;
+        if (ended || items >= item + take) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
+      if (item >= items) break;                   // ended, none left
+      const int64_t t = item + (take == 64 ? lane : lane / kFdbGroup);
+      if (t < items) {
         const int64_t at = items <= 0x7fffffff ? (int64_t)((uint32_t)t / (uint32_t)R) : t / R;
         const CandDev p = A.c[queue[q0 + at]];
         const int64_t dd = (int64_t)p.dm_index - A.dm_eps + (t - at * R);
-        if (dd >= 0 && dd < A.ndms) fdb_join_row(A, p, (int32_t)dd, gl, cid, labels);
+        if (dd >= 0 && dd < A.ndms) {
+          if (take == 64)
+            for_row(A, p, (int32_t)dd, [&](int32_t j) {
+              if (labels[j] < 0) labels[j] = cid;
+            });
+          else
+            fdb_join_row(A, p, (int32_t)dd, gl, cid, labels);
+        }
       }
     }
     __syncthreads();

@@ -1,5 +1,6 @@
-"""FDBSCAN with wide neighbourhoods: DM distances beyond the rows that there are.
-Labels, cluster count and query count equal the oracle's sequential FDBSCAN."""
+"""FDBSCAN with wide neighbourhoods: DM distances beyond the rows that there are,
+joins that fall behind the levels and go over to a lane a row.  Labels, cluster
+count and query count equal the oracle's sequential FDBSCAN."""
 import numpy as np
 import pytest
 import torch
@@ -22,6 +23,11 @@ def _list(n, rows, span):
 
 
 @pytest.mark.parametrize("n,rows,span,te,de,mp", [
+    (3000, 200, 400, 3, 199, 5),       # every row in reach: 399 rows a neighbourhood
+    (3000, 200, 400, 3, 100, 60),      # some points core, most not
+    (2000, 3, 900, 4, 2, 4),           # five rows a neighbourhood: less than a wave's lanes
+    (1500, 64, 6000, 2, 63, 2),        # many small clusters
+    (1200, 32, 90, 40, 31, 4),         # one cloud, long runs
     (700, 1, 3000, 5, 65535, 3),       # one row
     (40, 5, 50, 3, 70, 3),
     (900, 30, 400, 3, 30, 4),
@@ -54,3 +60,13 @@ def test_rows_out_of_reach_cost_nothing():
     rec, buf = _list(2400, 64, 8000)
     last, beyond = (_ms(lambda: A.fdbscan_candidates(buf, len(rec), 64, 16, de, 2.0, 5)) for de in (63, 10000))
     assert beyond < 1.5 * last
+
+
+def test_wide_joins_keep_the_lanes_busy():
+    """Expanding 4090 points with all 400 rows in reach against DBSCAN of the
+    same list on the whole GPU: 10 times as long, 12 before joins went by groups
+    of lanes, 49 with groups alone."""
+    A = api()
+    rec, buf = _list(6000, 400, 4000)
+    args = (buf, len(rec), 400, 4, 399, 2.0, 5)
+    assert _ms(lambda: A.fdbscan_candidates(*args)) < 24 * _ms(lambda: A.cluster_candidates(*args))
