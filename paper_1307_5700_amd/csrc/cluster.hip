@@ -380,11 +380,11 @@ __device__ inline void fdb_join_row(const ClusterArgs& A, const CandDev& p, int3
 // Groups keep few rows in flight, which is enough while the joins follow the
 // levels; with wide neighbourhoods (a large dm_eps) they fall behind, and from
 // kFdbBacklog waiting rows on a wave takes 64 of them, one to a lane: a row takes
-// longer there, but eight times as many are under way.  15048 detections in 640 DM rows, all rows in reach, 120 -> 27.9 ms; 2390 in 64
-// rows, all in reach, 1.34 -> 1.00 ms (limits of 128, 512 and 1024 rows: 0.96,
-// 1.11 and 1.15 ms); with few rows in reach as before.  Runs of hundreds of
-// points are slower so: 2390 in 64 rows, 9 rows of 8001 samples in reach, 0.30 ->
-// 0.36 ms.
+// longer there, but eight times as many are under way.  15048 detections in 640
+// DM rows, all rows in reach, 120 -> 27.9 ms; 2390 in 64 rows, all in reach, 1.34
+// -> 1.00 ms (limits of 128, 512 and 1024 rows: 0.96, 1.11 and 1.15 ms); with few
+// rows in reach as before.  Runs of hundreds of points are slower so: 2390 in 64
+// rows, 9 rows of 8001 samples in reach, 0.30 -> 0.36 ms.
 constexpr int kFdbScan = 4;
 constexpr int kFdbItems = 64 / kFdbGroup;
 constexpr int kFdbBacklog = 256;

@@ -132,9 +132,11 @@ __device__ inline void issue(Staged<TIN, RING>& s, const DedispArgs& A, const TI
 // read from `row` on, the quad at sample q + 256 * k is returned, and quads
 // past the n samples read as 0 without a fetch.  Neither bounds nor 64-bit
 // addresses take vector instructions, whose issue is what the tiled kernel is
-// shortest of (74 % busy): single shots without a ring, 1024 channels x 640
-// DMs x 65536 f32 samples, cleaned, with normalisation and detection 2.436 ->
-// 2.410 ms; 4096 channels x 2048 DMs in f16 20.24 -> 20.14 ms.
+// shortest of (72 % busy).  Against loads by pointers, 110 shapes of 64 to 4096
+// channels, the two timed in turn and two runs of one 0.3 % apart: cleaned f32
+// 0 to 2 % faster (1024 channels x 640 DMs x 65536 samples, with normalisation
+// and detection 2.436 -> 2.410 ms), cleaned f16 1 to 3 %, cleaned u8 1 to 3 %
+// and 3 to 8 % in tiles of at most 16 DMs, f16 without cleaning 0 to 6 %.
 template <typename TIN>
 __device__ inline typename Quad<TIN>::Raw quad_buffer_load(const TIN* row, uint32_t n, uint32_t q, int k) {
   const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<TIN*>(row), 0, n * (uint32_t)sizeof(TIN), 0x00020000);
@@ -418,6 +420,13 @@ __device__ __forceinline__ void dedisp_tile(const DedispArgs& A, const int32_t* 
   // kernel, whose tile loop leaves few registers, trims only cleaned 8-bit
   // rows (its other variants would spill).
   constexpr bool TRIM = NCP == 4 && WPR == 1 && (SKIP_IDLE || (sizeof(TIN) == 1 && CLEAN));
+  // Quads come by buffer loads where no sample lies in a ring, except where
+  // that measured no faster than pointers: f32 rows without cleaning (16 shapes
+  // within 0.5 %, 1024 channels x 640 DMs x 32768 samples 985 us by pointers and
+  // 989), and cleaned f16 rows in tiles of 8 DMs x 512 outputs (six more vector
+  // registers; 11 shapes 0.3 to 1.1 % slower, by pointers within 0.5 %).
+  constexpr bool kPointers = RING || (!CLEAN && sizeof(TIN) == 4) ||
+                             (CLEAN && sizeof(TIN) == 2 && NW == 4 && G == 2 && Q == 2);
   int rowq[NSET][RPW];   // quads staged of the row (live: m < rowq)
   float fitn[NSET][RPW]; // bandpass value of the row being staged (loaded with its quads)
   int32_t rowt[NSET][RPW]; // chunk index of the staged row's window start (uniform)
@@ -474,9 +483,7 @@ __device__ __forceinline__ void dedisp_tile(const DedispArgs& A, const int32_t* 
         const float* ringrow = RING ? A.ring + (int64_t)c * A.R : nullptr;
         load_meta(rm[S][rr], c, a);
         if (CLEAN) fitn[S][rr] = fit32[c + lane * A.zero];
-        // (f32 rows without cleaning gain nothing: 985 us by pointers, 989 by
-        // descriptors for 1024 channels x 640 DMs x 32768 samples)
-        if constexpr (RING || (!CLEAN && sizeof(TIN) == 4)) {
+        if constexpr (kPointers) {
 #pragma unroll
           for (int k = 0; k < KM; ++k) {
             const int m = m0 + lane + 64 * k;
