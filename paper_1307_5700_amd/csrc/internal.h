@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "mx_rule.h"
+#include "split_rule.h"
 
 namespace mbtp {
 
@@ -191,6 +192,7 @@ constexpr int kSplitWaveFloats =
     kSplitBC * kSplitRS > kSplitDMs * kSplitBT ? kSplitBC * kSplitRS : kSplitDMs * kSplitBT;
 constexpr int kSplitMaxLds = (int)sizeof(float) * kSplitMaxWaves * kSplitWaveFloats;
 static_assert(kSplitDMs <= 2 * (kSplitMaxWaves / 2 + 1) && kSplitMaxLds <= 160 * 1024, "split kernel");
+static_assert(2 * kAccGroup == 64 && kSplitDMs == 8, "split_pays");
 hipError_t dedisp_split_prepare(int dtype);
 hipError_t launch_dedisp_split(int dtype, bool clean, bool ring, const DedispArgs& a, const float* fit32,
                                hipStream_t s);

@@ -688,24 +688,13 @@ bool uses_u8_int(const Prepared& P) {
          (reinterpret_cast<uintptr_t>(P.d_in) & 7) == 0 && P.ld % 8 == 0;
 }
 
-// Whether a launch takes the split kernel: the plan's tiles leave compute
-// units without work, and the split kernel's smaller ones are few per unit.
-// Its time grows with its tiles (0.06 us a channel for each per unit, 0.08 to
-// 0.1 with ring samples or a wide delay spread) while the tiled kernel's does
-// not: 0.32 us a channel for tiles of 48 DMs, 0.19 for the narrower tiles that
-// wide spreads leave.  So at most four per unit (1024 channels x 120 DMs x
-// 16384 samples, 3.5 a unit: 228 against 323 us; 1024 x 200, 5.7 a unit: 357
-// against 330), three with ring samples (768 x 100, 3.25 a unit, cleaned: 253
-// against 279; 1024 x 240, 3.75: 377 against 376), two for narrower tiles
-// (1024 x 240 at 1 DM a step, 1.2 a unit: 114 against 194; with a ring, 3.75:
-// 297 against 280).  With one or two channel groups there is nothing to split
-// (32 channels: 17 against 11 us; 64: 18 us either way; 128: 16 against 35).
-// Its byte offsets hold chunks of up to 2^28 samples.
+// Whether a launch takes the split kernel.  Its byte offsets hold chunks of up
+// to 2^28 samples.
 bool takes_split(const mb_plan& p, bool ring, const DedispArgs& a) {
   const int64_t tiles = (int64_t)a.n_dblocks * a.n_ttiles;
   const int64_t split = (int64_t)((a.ndms + kSplitDMs - 1) / kSplitDMs) * ((a.phase + a.nout + kSplitBT - 1) / kSplitBT);
-  const int64_t per_unit = p.tiling.BD() < 48 ? 2 : (ring ? 3 : 4);
-  return p.split && a.C > 2 * kAccGroup && a.L <= (int64_t(1) << 28) && tiles <= p.cus && split <= per_unit * p.cus;
+  return p.split && a.L <= (int64_t(1) << 28) &&
+         split_pays(a.C, a.ndms, dtype_bytes(p.desc.in_dtype), ring, p.tiling.BD(), tiles, split, p.cus);
 }
 
 // One launch of the float kernels; adds the one it takes to `kernels`.

@@ -74,11 +74,32 @@ def test_split_rows_hold_a_spread_of_253_samples(span):
 
 def test_split_takes_at_most_four_tiles_a_unit():
     units = torch.cuda.get_device_properties(0).multi_processor_count
-    p = _plan(80, 32, tsamp=400e-6)                          # four blocks of eight DMs
-    assert p.tiling["dm_block"] == 48
+    p = _plan(96, 64, tsamp=400e-6)                          # eight blocks of eight DMs
+    assert p.tiling["dm_block"] == 48 and units % 2 == 0
     for extra, name in ((0, "split"), (1, "tiled")):
-        p.execute(_input(80, 256 * units + extra + p.max_delay, "f32"))
+        p.execute(_input(96, 256 * units // 2 + extra + p.max_delay, "f32"))
         assert p.last_kernels == (name,)
+
+
+@pytest.mark.parametrize("C,nd,T,dtype,ring,name", [
+    (865, 11, 107108, "f32", False, "tiled"), (865, 11, 90000, "f32", False, "split"),   # 3.3 and 2.8 tiles a unit
+    (132, 12, 76106, "f32", False, "tiled"), (132, 12, 60000, "f32", False, "split"),    # 2.3, 1.8
+    (73, 96, 11264, "u8", True, "tiled"), (73, 96, 4096, "u8", True, "split"),           # 2.1, 0.8
+    (100, 96, 11264, "u8", True, "split"),
+], ids=str)
+def test_split_takes_fewer_tiles_of_few_dms_or_channels(C, nd, T, dtype, ring, name):
+    """Rows staged once per eight DMs, and workgroups of three waves, pay less
+    (on a GPU of 256 units)."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("sizes chosen for 256 compute units")
+    A = api()
+    p = _plan(C, nd, dtype, tsamp=400e-6)
+    x = _input(C, T + (0 if ring else p.max_delay), dtype)
+    beam = A.Beam(p) if ring else None
+    state = p.rfi_threshold(x) if ring else None             # cleaned: float kernels
+    for _ in range(3 if ring else 1):
+        p.execute(x, rfi_state=state, beam=beam)
+    assert p.last_kernels == (name,)
 
 
 def test_8_bit_chunks_report_their_kernels():
