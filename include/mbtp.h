@@ -85,8 +85,11 @@ typedef struct {
   double dm_start;     /* >= 0                                             */
   double dm_step;      /* >= 0                                             */
   mb_dtype in_dtype;   /* storage type of the filterbanks executed        */
-  int32_t tile_hint;   /* 0: library's choice; k > 0: k-th compiled
-                          dedispersion tiling (results do not depend on it) */
+  int32_t tile_hint;   /* 0: library's choice of kernel and tiling; k > 0:
+                          k-th compiled dedispersion tiling, for plans that
+                          are batched: such a plan leaves out the kernels
+                          MB_KERNEL_SPLIT and MB_KERNEL_MATRIX8, so alone it
+                          may be slower (results do not depend on it) */
   mb_rfi_params rfi;   /* used by rfi_threshold                           */
 } mb_plan_desc;
 

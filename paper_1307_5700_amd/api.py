@@ -54,7 +54,11 @@ def _alloc(nbytes: int, device) -> torch.Tensor:
 
 
 class Plan:
-    """Delay table + tiling for one beam's observing/survey parameters."""
+    """Delay table + tiling for one beam's observing/survey parameters.
+
+    tile_hint > 0 fixes the compiled tiling, which batched plans have to share;
+    such a plan takes neither the split nor the matrix-core kernel, so a beam
+    that runs alone is best planned without one."""
 
     def __init__(self, nchans, f_ch0_mhz, df_mhz, tsamp_s, ndms, dm_start, dm_step,
                  dtype: str = "f32", rfi: RfiConfig | None = None, tile_hint: int = 0,

@@ -2,7 +2,11 @@
 
 For a shape class (channels, DM grid, band, sampling time, storage type,
 cleaning on/off) it times every compiled tiling that fits, on a synthetic
-chunk on the current GPU, and keeps the fastest.  Results persist as JSON
+chunk on the current GPU, and keeps the fastest, beside the time of a plan
+without a tile_hint: such a plan also takes the kernels that a hinted one leaves
+out (split channel groups for small launches, matrix cores for 8-bit chunks
+without cleaning), so for a beam that runs alone it is often the faster choice.
+A hint is for plans that are batched.  Results persist as JSON
 (``$MBTP_AUTOTUNE_CACHE`` or ``~/.cache/mbtp/autotune.json``) keyed by the
 shape class and the GPU name, so a later run picks the tiling with no timing.
 """
@@ -52,8 +56,8 @@ def _synthetic_chunk(nchans: int, nsamps: int, dtype: str, device, seed: int) ->
 
 def time_tiling(plan_kwargs: dict, dtype: str, rfi: bool, nsamps: int, hint: int,
                 reps: int = 5, seed: int = 123, x: torch.Tensor | None = None) -> float | None:
-    """Milliseconds of one dedispersion launch with tiling ``hint``; None
-    when the tiling does not fit the plan."""
+    """Milliseconds of one dedispersion launch with tiling ``hint`` (0: of a
+    plan without one); None when the tiling does not fit the plan."""
     try:
         plan = A.Plan(dtype=dtype, tile_hint=hint, **plan_kwargs)
     except A.L.MbError:
@@ -79,21 +83,24 @@ def time_tiling(plan_kwargs: dict, dtype: str, rfi: bool, nsamps: int, hint: int
 
 def best_tiling(plan_kwargs: dict, dtype: str = "f32", rfi: bool = True, nsamps: int = 65536,
                 path: str | None = None, retune: bool = False) -> dict:
-    """The fastest compiled tiling for this shape class: {"hint", "ms", "all"}."""
+    """The fastest compiled tiling for this shape class: {"hint", "ms", "all",
+    "default_ms"}, the last the time of a plan without a hint, which is the one
+    to use for a beam that runs alone where it is less than "ms"."""
     path = path or cache_path()
     key = _key(plan_kwargs, dtype, rfi, nsamps)
     cache = _load(path)
-    if key in cache and not retune:
+    if "default_ms" in cache.get(key, {}) and not retune:
         return cache[key]
     dev = torch.device("cuda", torch.cuda.current_device())
     x = _synthetic_chunk(int(plan_kwargs["nchans"]), nsamps, dtype, dev, 123)
-    times = {h: time_tiling(plan_kwargs, dtype, rfi, nsamps, h, x=x) for h in range(1, A.num_tilings() + 1)}
+    times = {h: time_tiling(plan_kwargs, dtype, rfi, nsamps, h, x=x) for h in range(A.num_tilings() + 1)}
+    default = times.pop(0)
     del x
     ok = {h: t for h, t in times.items() if t is not None}
     if not ok:
         raise RuntimeError("no compiled tiling fits this plan")
     hint = min(ok, key=ok.get)
-    res = {"hint": hint, "ms": ok[hint], "all": {str(h): t for h, t in times.items()}}
+    res = {"hint": hint, "ms": ok[hint], "all": {str(h): t for h, t in times.items()}, "default_ms": default}
     cache = _load(path)
     cache[key] = res
     os.makedirs(os.path.dirname(path), exist_ok=True)
