@@ -370,24 +370,28 @@ __device__ inline void fdb_join_row(const ClusterArgs& A, const CandDev& p, int3
 // Dependent loads bound it (about 400 clocks each), so the chains are short
 // and overlap: which points a cluster expands follows from representatives
 // and query marks alone, so one wave follows those from level to level, with
-// no barrier, while the other 15 (and it, once done) join the members of the
-// neighbourhoods of the points it has queued, kFdbGroup lanes to a point and DM
-// row; the scan for the next start takes kFdbScan points a thread at a time, one
-// barrier a step (its minimum rotates over three slots, the next one cleared
-// while this one is in use).  53 858 detections, 640 DM rows, 5 pulses (27 clusters, 111
-// levels, 1532 points expanded): 837 -> 374 us.
+// no barrier, while the other 15 join the members of the neighbourhoods of the
+// points it has queued, kFdbGroup lanes to a point and DM row; the scan for the
+// next start takes kFdbScan points a thread at a time, one barrier a step (its
+// minimum rotates over three slots, the next one cleared while this one is in
+// use).  53 858 detections, 640 DM rows, 5 pulses (27 clusters, 111 levels, 1532
+// points expanded): 837 -> 374 us.
 //
 // Groups keep few rows in flight, which is enough while the joins follow the
-// levels; with wide neighbourhoods (a large dm_eps) they fall behind, and from
-// kFdbBacklog waiting rows on a wave takes 64 of them, one to a lane: a row takes
-// longer there, but eight times as many are under way.  15048 detections in 640
-// DM rows, all rows in reach, 120 -> 27.9 ms; 2390 in 64 rows, all in reach, 1.34
-// -> 1.00 ms (limits of 128, 512 and 1024 rows: 0.96, 1.11 and 1.15 ms); with few
-// rows in reach as before.  Runs of hundreds of points are slower so: 2390 in 64
-// rows, 9 rows of 8001 samples in reach, 0.30 -> 0.36 ms.
+// levels; with wide neighbourhoods they fall behind.  So from kFdbWide DM rows in
+// reach on, waves take rows from a counter, the expanding wave too once its levels
+// are done, and with kFdbBacklog rows waiting 64 at a time, one to a lane: a row
+// takes longer there, but eight times as many are under way.  15048 detections in
+// 640 DM rows, all rows in reach, 120 -> 27.9 ms; 2390 in 64 rows, all in reach,
+// 1.34 -> 1.00 ms (limits of 128, 512 and 1024 rows: 0.96, 1.11 and 1.15 ms).  With
+// fewer rows in reach the counter costs more than it gives: 18935 detections, 640
+// rows, 9 / 25 / 33 / 49 rows of 61 samples in reach, 0.48 / 5.4 / 8.1 / 10.5 ms in
+// turn, 0.51 / 5.6 / 8.4 / 9.4 by the counter; 2971 detections, 64 rows, 9 / 13 / 25
+// rows of 33 samples, 1.07 / 0.54 / 0.90 and 1.10 / 0.46 / 0.42 ms.
 constexpr int kFdbScan = 4;
 constexpr int kFdbItems = 64 / kFdbGroup;
 constexpr int kFdbBacklog = 256;
+constexpr int kFdbWide = 24;
 
 __global__ __launch_bounds__(1024) void fdb_expand_kernel(ClusterArgs A, const int32_t* __restrict__ cnt,
                                                           const uint64_t* __restrict__ keys,
@@ -494,41 +498,57 @@ __global__ __launch_bounds__(1024) void fdb_expand_kernel(ClusterArgs A, const i
     }
     // every member of their neighbourhoods that carries no label joins the
     // cluster (all writers write cid): (point, DM row) items, as they come; the
-    // expanding wave waits for nothing, so its end always comes, and then it
-    // joins the rest with the others
-    for (;;) {
-      // a wave takes as many items as it has groups, or lanes
-      int64_t items = (__hip_atomic_load(&s_queued, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) - q0) * R;
-      int64_t item = 0;
-      int take = kFdbItems;
-      if (lane == 0) {
-        const int64_t taken = (int64_t)__hip_atomic_load(&s_taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (items - taken >= kFdbBacklog) take = 64;
-        item = (int64_t)atomicAdd(&s_taken, (unsigned long long)take);
-      }
-      take = __builtin_amdgcn_readfirstlane(take);
-      item = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(item >> 32)) << 32) |
-                       (uint32_t)__builtin_amdgcn_readfirstlane((int)item));
+    // expanding wave waits for nothing, so its end always comes
+    auto wait_for = [&](int64_t last) {
       for (;;) {
         const bool ended = __hip_atomic_load(&s_ended, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == ncl;
-        items = (__hip_atomic_load(&s_queued, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) - q0) * R;
-        if (ended || items >= item + take) break;
+        const int64_t items =
+            (__hip_atomic_load(&s_queued, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) - q0) * R;
+        if (ended || items >= last) return items;
         __builtin_amdgcn_s_sleep(1);
       }
-      if (item >= items) break;                   // ended, none left
-      const int64_t t = item + (take == 64 ? lane : lane / kFdbGroup);
+    };
+    auto join = [&](int64_t item, int64_t items, bool lanes) {
+      const int64_t t = item + (lanes ? lane : lane / kFdbGroup);
       if (t < items) {
         const int64_t at = items <= 0x7fffffff ? (int64_t)((uint32_t)t / (uint32_t)R) : t / R;
         const CandDev p = A.c[queue[q0 + at]];
         const int64_t dd = (int64_t)p.dm_index - A.dm_eps + (t - at * R);
         if (dd >= 0 && dd < A.ndms) {
-          if (take == 64)
+          if (lanes)
             for_row(A, p, (int32_t)dd, [&](int32_t j) {
               if (labels[j] < 0) labels[j] = cid;
             });
           else
             fdb_join_row(A, p, (int32_t)dd, gl, cid, labels);
         }
+      }
+    };
+    if (R < kFdbWide) {
+      // waves 1 to 15 take kFdbItems items in turn
+      for (int64_t item = wave > 0 ? (int64_t)(wave - 1) * kFdbItems : INT64_MAX; item < INT64_MAX;
+           item += 15 * kFdbItems) {
+        const int64_t items = wait_for(item + kFdbItems);
+        if (item >= items) break;                 // ended, none left
+        join(item, items, false);
+      }
+    } else {
+      // a wave takes as many items as it has groups, or lanes
+      for (;;) {
+        int64_t item = 0;
+        int take = kFdbItems;
+        if (lane == 0) {
+          const int64_t queued = __hip_atomic_load(&s_queued, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) - q0;
+          const int64_t taken = (int64_t)__hip_atomic_load(&s_taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (queued * R - taken >= kFdbBacklog) take = 64;
+          item = (int64_t)atomicAdd(&s_taken, (unsigned long long)take);
+        }
+        take = __builtin_amdgcn_readfirstlane(take);
+        item = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(item >> 32)) << 32) |
+                         (uint32_t)__builtin_amdgcn_readfirstlane((int)item));
+        const int64_t items = wait_for(item + take);
+        if (item >= items) break;                 // ended, none left
+        join(item, items, take == 64);
       }
     }
     __syncthreads();

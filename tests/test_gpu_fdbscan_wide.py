@@ -25,7 +25,8 @@ def _list(n, rows, span):
 @pytest.mark.parametrize("n,rows,span,te,de,mp", [
     (3000, 200, 400, 3, 199, 5),       # every row in reach: 399 rows a neighbourhood
     (3000, 200, 400, 3, 100, 60),      # some points core, most not
-    (2000, 3, 900, 4, 2, 4),           # five rows a neighbourhood: less than a wave's lanes
+    (2000, 30, 900, 4, 11, 4),         # 23 rows a neighbourhood: taken in turn
+    (2000, 30, 900, 4, 12, 4),         # 25: from the counter
     (1500, 64, 6000, 2, 63, 2),        # many small clusters
     (1200, 32, 90, 40, 31, 4),         # one cloud, long runs
     (700, 1, 3000, 5, 65535, 3),       # one row
