@@ -28,20 +28,26 @@
 // transpose 4 x 4 bytes at a time and write cells of 16 channels.  Eight
 // consumer waves own 144 columns of a DM group each, as 9 tiles: column
 // 9 m + j is row m of tile j.  With that stride, tile j at shift s reads the
-// cells that tile j + 1 reads at shift s - 1, so S shifts of 9 tiles cost
-// 9 + S - 1 operand reads instead of 9 S, and the odd stride keeps the reads
-// free of bank conflicts.  At the end of a partial sum the columns go through
-// LDS, and each wave adds four DMs' rows, each from its own offset, to 32-bit
-// sums in registers.  Two staged steps alternate, one barrier per step.
+// cells that tile j + 1 reads at shift s - 1, so shifts taken together share
+// operand reads: 12 for the first four shifts of 9 tiles and 10 for each two
+// after them, instead of 9 a shift (fewer than four are taken as four, an odd
+// one as two).  The odd stride spreads one quarter's reads over all banks.  At
+// the end of a partial sum the columns go through LDS, and each wave adds four
+// DMs' rows, each from its own offset, to 32-bit sums in registers.  Two staged
+// steps alternate, one barrier per step.
 //
-// What bounds it: matrix and vector instructions of a SIMD hardly overlap
-// (a probe: about one vector instruction per 16x16x64 product), and a step
-// has about 160 products (17 clocks each) and 550 other vector instructions
-// (2.6 clocks) per SIMD, beside 0.4 MB of LDS traffic per CU.  Measured on the
-// 1024-channel x 65536-sample x 640-DM beam: 0.46 ms (0.52 ms on uniformly
-// random bytes) against 1.75 ms for the packed 16-bit add kernel, 85 against
-// 22 x 10^12 adds/s; 4096 channels x 1024 DMs: 1.75 against 9.83 ms; 512
-// channels x 320 DMs x 16384 samples: 0.067 against 0.134 ms.
+// What bounds it (counters on the 1024-channel x 65536-sample x 640-DM beam):
+// no one unit.  A step has 161 products of 16 clocks and 560 other vector
+// instructions of 2.6 a SIMD, which hardly overlap (a probe: about one vector
+// instruction per product): 36 % and 21 % of the cycles.  The LDS is busy for
+// 60 % of them, half of that with bank conflicts (31 % of all cycles): a
+// producer lane writes its 16 bytes 64 bytes from the next lane's, so lanes
+// four apart meet, and an operand read spans four quarters whose first cells
+// differ by any amount.  Few waves hide the rest, waits for LDS and barriers.
+// 0.46 to 0.49 ms (0.52 on uniformly random bytes) against 1.75 ms for the
+// packed 16-bit add kernel, 80 against 22 x 10^12 adds/s; 4096 channels x 1024
+// DMs: 1.75 against 9.83 ms; 512 channels x 320 DMs x 16384 samples: 0.067
+// against 0.134 ms.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>

@@ -225,9 +225,11 @@ void u8_geometry(mb_plan& p) {
 
 // Decides whether the plan uses the matrix-core kernel and builds its tables on
 // the device: its columns must hold the tile's outputs and the delay spread of
-// 16 DMs, its staged cells the spread of 32, and the table 16 shifts (at the
-// least tile, 128 outputs, and the most shifts it forms about 25 x 10^12 adds/s
-// by its instruction counts, against 22 for the packed-add kernel at its best).
+// 16 DMs, its staged cells the spread of 32, and the table 16 shifts.  At 16
+// shifts it is still the faster one: 129 channels x 40 DMs x 59498 outputs 25
+// against 39 us for the packed-add kernel, 513 x 48 x 57896 in tiles of 452
+// outputs 72 against 136 (plans whose rows fit the packed-add kernel have tiles of
+// 300 outputs and more).
 // The tables take 2 bytes per DM and channel, so what the delays need is found
 // first; a plan whose tables do not fit in memory keeps the packed-add kernel.
 hipError_t setup_mx(mb_plan& p) {
